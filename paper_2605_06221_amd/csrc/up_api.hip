@@ -210,10 +210,16 @@ void choose_geometry(Problem* pb, const int32_t* cu, const int32_t* cu_k = nullp
   pb->key_block_slots = pb->Tk / g1.kb + pb->R;
   pb->max_key_blocks = (longest_k + g1.kb - 1) / g1.kb;
   if (!pb->has_ctx) {
-    pb->key_block2 = g1.kb;
+    // Head rows of 128 bytes: pass 2 takes 256 keys per work-group.  Two of them share a CU (40 KB of LDS and
+    // 109 registers each; of the 16-wave one only one fits), so one's key loads and barriers hide behind the
+    // other's matrix work: three ragged prompts of 43876 tokens, 32/8 heads, 155.6 -> 144.5 us a call.  Head
+    // dimension 128 stays at 512: 584 us there and 627 at 256 with two per CU (131072 tokens, 40/8 heads),
+    // twice the row staging for half the keys.  The partial
+    // column sums never need more room than at 512: (T/256 + R) * 256 <= (T/512 + R) * 512 for R >= 1.
+    pb->key_block2 = !pb->qk_is_f32 && pb->head_dim == 64 ? 256 : g1.kb;
     pb->split2 = g1.split;
     pb->spare2 = 1;
-    pb->key_block_slots2 = pb->key_block_slots;
+    pb->key_block_slots2 = pb->T / pb->key_block2 + pb->R;
   } else {
     // pass 2 sweeps only the key blocks that hold keys of the tokens: from the block of the
     // first token's key (not aligned with the tokens: one more slot per sequence) to the last

@@ -361,6 +361,18 @@ def test_fused_head_dims_64_and_256_bit_exact(head_dim):
     _assert_fused_exact(w, b, oracle_run(w))
 
 
+@pytest.mark.parametrize("lengths", [[256], [257, 511], [512 * 12 + 1], [255, 1, 513, 40 * 512, 31, 37 * 512 + 257]])
+def test_fused_head_dim_64_at_key_block_edges_bit_exact(lengths):
+    """Pass 2 takes 256 keys per work-group at head dimension 64 while pass 1 may take 512: lengths at
+    the edges of either, alone and ragged, with the heads of a key block split or not."""
+    _say("fused head_dim 64 edges", lengths)
+    w = workloads.make_custom(name="hd64e", seed=21, lengths=lengths, keep_ratio=[0.4] * len(lengths), hidden_dim=64,
+                              num_q_heads=8, num_kv_heads=2, block_size=32, n_obs=96, head_dim=64)
+    b = DeviceBatch(w)
+    b.fused()
+    _assert_fused_exact(w, b, oracle_run(w))
+
+
 def test_scores_from_fp32_operands_head_dim_64():
     _say("score fp32 head_dim 64")
     w = workloads.make_custom(name="f32hd", seed=16, lengths=[1, 130, 0, 700, 2100], keep_ratio=[0.5] * 5,
