@@ -160,10 +160,10 @@ int check_ratio(const up_params* p, const float* ratio_host) {
 // one work-group per CU; launches of a few rounds are split further (below).
 //   live(kb)  key blocks of kb keys that have work in this pass
 //   grid(kb)  slots of the launch (the live ones plus the spares that sit between them)
+constexpr int kCUs = 256, kEnough = 224;
 struct PassGeometry { int kb, split; };
 template <class Live, class Grid>
 PassGeometry pass_geometry(const Problem& pb, long long units_per_head, Live live, Grid grid) {
-  constexpr int kCUs = 256, kEnough = 224;
   int kb = narrow_only(pb) ? 256 : 512;
   long long nb = live(kb);
   int split = 1;
@@ -184,6 +184,31 @@ PassGeometry pass_geometry(const Problem& pb, long long units_per_head, Live liv
   if (slots * split > kCUs)
     while (can_double() && nb * split < 6 * kCUs && (pb.Hkv / (2 * split)) * units_per_head >= 8) split *= 2;
   return PassGeometry{kb, split};
+}
+
+// Pass 2 without earlier context takes pass 1's split, and its key block but for one case: head rows of 128
+// bytes (D = 64 in bf16) in 256-key work-groups where pass 1 has 512.  Two of these share a CU (70656 bytes
+// of LDS and 109 registers each; the 16-wave one has its CU to itself), so one's key loads and barriers hide
+// behind the other's matrix work, and a round that is not full costs less: three ragged prompts of 43876 tokens,
+// 32/8 heads, 153.4 -> 141.2 us a call; batches of more than one round up to 16 % (25 % with the log-sum-exp given)
+// and none slower by more than the runs of one side differ, 131072 tokens in one unsplit round 0.2 to 8 %.
+// 512 keys stay where their launch is one round already, filled like the split aims at, and there is little to hide: 256
+// keys then only stage the query rows twice.  Measured 512 -> 256 there: 32768 tokens split four ways, 40/8 heads,
+// 122.6 -> 123.9 us; 30000 tokens 87.9 -> 90.8; two of 30000 with the log-sum-exp given 70.7 -> 74.6; unsplit
+// with sixteen staging units a head (window 512, 122000 tokens, log-sum-exp given) 413.7 -> 429.0.  One round counts the
+// slots, as above; blocks of sequences short enough to be kept whole fill none of it: 64 decode rows before 28000
+// tokens take 135.4 us at 512 and 122.3 at 256, 38 before 40960 (160 full work-groups, window 512) 442.8 and 437.6.
+// The partial column sums never need more room than at 512: (T/256 + R) * 256 <= (T/512 + R) * 512 for R >= 1.
+int pass2_key_block(const Problem& pb, const PassGeometry& g1, long long units_per_head, const int32_t* cu) {
+  if (pb.qk_is_f32 || pb.head_dim != 64 || g1.kb != 512) return g1.kb;
+  long long scored = 0;
+  for (int r = 0; r < pb.R; ++r) {
+    const int N = cu[r + 1] - cu[r];
+    if (N > (long long)pb.n_sink + pb.n_obs) scored += (N + 511) / 512;
+  }
+  const long long slots = pb.R == 1 ? scored : (long long)pb.T / 512 + pb.R;
+  const bool one_round = slots * g1.split <= kCUs && scored * g1.split >= kEnough;
+  return one_round && (g1.split > 1 || units_per_head >= 8) ? 512 : 256;
 }
 
 void choose_geometry(Problem* pb, const int32_t* cu, const int32_t* cu_k = nullptr) {
@@ -210,13 +235,7 @@ void choose_geometry(Problem* pb, const int32_t* cu, const int32_t* cu_k = nullp
   pb->key_block_slots = pb->Tk / g1.kb + pb->R;
   pb->max_key_blocks = (longest_k + g1.kb - 1) / g1.kb;
   if (!pb->has_ctx) {
-    // Head rows of 128 bytes: pass 2 takes 256 keys per work-group.  Two of them share a CU (40 KB of LDS and
-    // 109 registers each; of the 16-wave one only one fits), so one's key loads and barriers hide behind the
-    // other's matrix work: three ragged prompts of 43876 tokens, 32/8 heads, 155.6 -> 144.5 us a call.  Head
-    // dimension 128 stays at 512: 584 us there and 627 at 256 with two per CU (131072 tokens, 40/8 heads),
-    // twice the row staging for half the keys.  The partial
-    // column sums never need more room than at 512: (T/256 + R) * 256 <= (T/512 + R) * 512 for R >= 1.
-    pb->key_block2 = !pb->qk_is_f32 && pb->head_dim == 64 ? 256 : g1.kb;
+    pb->key_block2 = pass2_key_block(*pb, g1, units_per_head, cu);
     pb->split2 = g1.split;
     pb->spare2 = 1;
     pb->key_block_slots2 = pb->T / pb->key_block2 + pb->R;

@@ -26,8 +26,8 @@ struct Problem {
   int key_block;              // keys per work-group: 256 or 512
   int key_block_slots;        // Tk / key_block + R: key blocks of all sequences (an upper bound)
   int split;                  // work-groups per key block: each sweeps Hkv / split kv heads
-  // pass 2 (column sums) runs over the tokens' own keys; without earlier context its geometry is
-  // that of pass 1
+  // pass 2 (column sums) runs over the tokens' own keys; without earlier context its head split is that of
+  // pass 1, and so is its key block except at head dimension 64 in bf16 (256 where pass 1 may take 512)
   int key_block2, split2;
   int spare2;                 // slots per sequence beyond N / key_block2: 1, or 2 with earlier context
                               // (the tokens' first key is then not aligned with a key block)
