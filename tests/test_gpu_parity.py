@@ -8,6 +8,7 @@ import torch
 import oracle
 import paper_2605_06221_amd as up
 import workloads
+from geometry_cases import HEAD_64
 from gpu_util import DeviceBatch, dev_bf16, host_bits, oracle_run, score_margin_report
 
 pytestmark = pytest.mark.gpu
@@ -333,7 +334,7 @@ def _many_lengths(seed, count):
 ])
 def test_scores_head_dims_64_and_256_match_oracle(head_dim, case):
     """Head dimensions other than 128: four (64) or sixteen (256) matrix steps per tile, the
-    latter in 256-key work-groups only; "many" reaches the 512-key work-groups for 64."""
+    latter in 256-key work-groups only; "many" reaches the 512-key work-groups for 64 in pass 1."""
     lengths = _many_lengths(7, 230) if case["lengths"] == "many" else case["lengths"]
     _say("score head_dim", head_dim, case if case["lengths"] != "many" else "many sequences")
     w = workloads.make_custom(name="hd", seed=14, lengths=lengths, keep_ratio=[0.5] * len(lengths),
@@ -363,11 +364,24 @@ def test_fused_head_dims_64_and_256_bit_exact(head_dim):
 
 @pytest.mark.parametrize("lengths", [[256], [257, 511], [512 * 12 + 1], [255, 1, 513, 40 * 512, 31, 37 * 512 + 257]])
 def test_fused_head_dim_64_at_key_block_edges_bit_exact(lengths):
-    """Pass 2 takes 256 keys per work-group at head dimension 64 while pass 1 may take 512: lengths at
-    the edges of either, alone and ragged, with the heads of a key block split or not."""
+    """Lengths at the edges of 256- and 512-key blocks, alone and ragged: batches of few key blocks, which both
+    passes take in 256-key work-groups with the heads split in two."""
     _say("fused head_dim 64 edges", lengths)
     w = workloads.make_custom(name="hd64e", seed=21, lengths=lengths, keep_ratio=[0.4] * len(lengths), hidden_dim=64,
                               num_q_heads=8, num_kv_heads=2, block_size=32, n_obs=96, head_dim=64)
+    b = DeviceBatch(w)
+    b.fused()
+    _assert_fused_exact(w, b, oracle_run(w))
+
+
+@pytest.mark.parametrize("name", HEAD_64)
+def test_fused_head_dim_64_in_every_launch_geometry_bit_exact(name):
+    """Every pairing of 512- and 256-key work-groups in the two passes, with the heads of a key block split and
+    not, without and after earlier context (that each batch gets its geometry is a test of the host side)."""
+    batch, pass1, pass2 = HEAD_64[name]
+    _say("fused head_dim 64 geometry", name, "pass 1", pass1, "pass 2", pass2)
+    n = len(batch["lengths"])
+    w = workloads.make_custom(name="hd64g", seed=22, keep_ratio=[0.4] * n, hidden_dim=64, block_size=32, head_dim=64, **batch)
     b = DeviceBatch(w)
     b.fused()
     _assert_fused_exact(w, b, oracle_run(w))
