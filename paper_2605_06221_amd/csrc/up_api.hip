@@ -188,13 +188,14 @@ PassGeometry pass_geometry(const Problem& pb, long long units_per_head, Live liv
 
 // Pass 2 without earlier context takes pass 1's split, and its key block but for one case: head rows of 128
 // bytes (D = 64 in bf16) in 256-key work-groups where pass 1 has 512.  Two of these share a CU (70656 bytes
-// of LDS and 109 registers each; the 16-wave one has its CU to itself), so one's key loads and barriers hide
-// behind the other's matrix work, and a round that is not full costs less: three ragged prompts of 43876 tokens,
-// 32/8 heads, 153.4 -> 141.2 us a call; batches of more than one round up to 16 % (25 % with the log-sum-exp given)
-// and none slower by more than the runs of one side differ, 131072 tokens in one unsplit round 0.2 to 8 %.
-// 512 keys stay where their launch is one round already, filled like the split aims at, and there is little to hide: 256
-// keys then only stage the query rows twice.  Measured 512 -> 256 there: 32768 tokens split four ways, 40/8 heads,
-// 122.6 -> 123.9 us; 30000 tokens 87.9 -> 90.8; two of 30000 with the log-sum-exp given 70.7 -> 74.6; unsplit
+// of LDS and 109 registers each; the 16-wave one has its CU to itself), so a round that is not full costs
+// half as much, and at a switch of kv head one's key loads run beside the other's tiles: three ragged prompts of 43876
+// tokens, 32/8 heads, 344 work-groups on 256 places, 153.4 -> 141.2 us a call; batches of more than one round up to
+// 16 % (25 % with the log-sum-exp given) and none slower by more than the runs of one side differ; 131072 tokens in
+// one unsplit round (seven switches) 0.2 to 8 %.
+// 512 keys stay where their launch is one round already, filled like the split aims at, and switches are few or the
+// units between them many: 256 keys then only stage the query rows twice.  Measured 512 -> 256 there: 32768 tokens
+// split four ways, 40/8 heads, 122.6 -> 123.9 us; 30000 tokens 87.9 -> 90.8; two of 30000 with the log-sum-exp given 70.7 -> 74.6; unsplit
 // with sixteen staging units a head (window 512, 122000 tokens, log-sum-exp given) 413.7 -> 429.0.  One round counts the
 // slots, as above; blocks of sequences short enough to be kept whole fill none of it: 64 decode rows before 28000
 // tokens take 135.4 us at 512 and 122.3 at 256, 38 before 40960 (160 full work-groups, window 512) 442.8 and 437.6.
