@@ -199,7 +199,8 @@ PassGeometry pass_geometry(const Problem& pb, long long units_per_head, Live liv
 // with sixteen staging units a head (window 512, 122000 tokens, log-sum-exp given) 413.7 -> 429.0.  One round counts the
 // slots, as above; blocks of sequences short enough to be kept whole fill none of it: 64 decode rows before 28000
 // tokens take 135.4 us at 512 and 122.3 at 256, 38 before 40960 (160 full work-groups, window 512) 442.8 and 437.6.
-// The partial column sums never need more room than at 512: (T/256 + R) * 256 <= (T/512 + R) * 512 for R >= 1.
+// The partial column sums need no more room at 256 than at 512, (T/256 + R) * 256 <= (T/512 + R) * 512 for R >= 1, so
+// a workspace that holds them at 256 only takes that form (choose_geometry).
 int pass2_key_block(const Problem& pb, const PassGeometry& g1, long long units_per_head, const int32_t* cu) {
   if (pb.qk_is_f32 || pb.head_dim != 64 || g1.kb != 512) return g1.kb;
   long long scored = 0;
@@ -212,7 +213,8 @@ int pass2_key_block(const Problem& pb, const PassGeometry& g1, long long units_p
   return one_round && (g1.split > 1 || units_per_head >= 8) ? 512 : 256;
 }
 
-void choose_geometry(Problem* pb, const int32_t* cu, const int32_t* cu_k = nullptr) {
+// (room: bytes of workspace at hand; the plan asks for what the faster form needs)
+void choose_geometry(Problem* pb, const int32_t* cu, const int32_t* cu_k, size_t room) {
   const int32_t* ck = cu_k != nullptr ? cu_k : cu;     // pass 1 sweeps every key
   pb->has_ctx = cu_k != nullptr;
   pb->Tk = ck[pb->R];
@@ -240,6 +242,10 @@ void choose_geometry(Problem* pb, const int32_t* cu, const int32_t* cu_k = nullp
     pb->split2 = g1.split;
     pb->spare2 = 1;
     pb->key_block_slots2 = pb->T / pb->key_block2 + pb->R;
+    if (!pb->qk_is_f32 && pb->head_dim == 64 && pb->key_block2 == 512 && workspace_layout(*pb).total > room) {
+      pb->key_block2 = 256;
+      pb->key_block_slots2 = pb->T / 256 + pb->R;
+    }
   } else {
     // pass 2 sweeps only the key blocks that hold keys of the tokens: from the block of the
     // first token's key (not aligned with the tokens: one more slot per sequence) to the last
@@ -281,7 +287,8 @@ long long host_total_kept(const Problem& pb, const int32_t* cu, const int32_t* c
 // (cu_k_dev / cu_k_host are nullptr for sequences whose keys are their own tokens' keys)
 
 int plan_impl(const up_params* p, const int32_t* cu_host, const int32_t* cu_k_host, bool ctx,
-              const float* ratio_host, int32_t* new_cu_host, int64_t* total_kept, size_t* workspace_bytes) {
+              const float* ratio_host, int32_t* new_cu_host, int64_t* total_kept, size_t* workspace_bytes,
+              size_t room = SIZE_MAX) {
   Problem pb;
   const bool want_ws = workspace_bytes != nullptr;
   int st = check_params(p, want_ws, false, &pb);
@@ -291,7 +298,7 @@ int plan_impl(const up_params* p, const int32_t* cu_host, const int32_t* cu_k_ho
   if ((st = check_ratio(p, ratio_host)) != UP_OK) return st;
   const long long total = host_total_kept(pb, cu_host, cu_k_host, ratio_host, new_cu_host);
   if (total_kept) *total_kept = total;
-  if (want_ws) choose_geometry(&pb, cu_host, cu_k_host);
+  if (want_ws) choose_geometry(&pb, cu_host, cu_k_host, room);
   if (want_ws) *workspace_bytes = workspace_layout(pb).total;
   return UP_OK;
 }
@@ -347,7 +354,7 @@ int score_impl(const up_params* p, const void* q, const void* k, const int32_t* 
   if ((st = check_key_side(p, cu_host, ks)) != UP_OK) return st;
   if (lse != nullptr && lse_stride < pb.T) return UP_ERR_SHAPE;      // the heads of lse would overlap
   if (!aligned16(q) || !aligned16(k)) return UP_ERR_ALIGN;
-  choose_geometry(&pb, cu_host, cu_k_host);
+  choose_geometry(&pb, cu_host, cu_k_host, workspace_bytes);
   if (pb.T > 0 && (workspace == nullptr || workspace_bytes < workspace_layout(pb).total)) return UP_ERR_WORKSPACE;
   if (pb.T > 0 && (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return UP_ERR_ALIGN;
   hipStream_t s = (hipStream_t)stream;
@@ -403,7 +410,7 @@ int fused_impl(const up_params* p, const void* q, const void* k, const void* hid
   if (lse != nullptr && lse_stride < pb.T) return UP_ERR_SHAPE;      // the heads of lse would overlap
   if (!aligned16(q) || !aligned16(k) || !aligned16(hidden) || !aligned16(hidden_out))
     return UP_ERR_ALIGN;
-  choose_geometry(&pb, cu_host, cu_k_host);
+  choose_geometry(&pb, cu_host, cu_k_host, workspace_bytes);
   const Workspace w = workspace_layout(pb);
   if (pb.T > 0 && (workspace == nullptr || workspace_bytes < w.total)) return UP_ERR_WORKSPACE;
   if (pb.T > 0 && (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return UP_ERR_ALIGN;
@@ -500,7 +507,7 @@ int fused_top_p_impl(const up_params* p, const void* q, const void* k, const voi
   for (int r = 0; r < p->num_seqs; ++r)
     if ((cu_host[r + 1] - cu_host[r] + pb.G - 1) / pb.G > kMaxTopPBlocks) return UP_ERR_UNSUPPORTED;
   if (!aligned16(q) || !aligned16(k) || !aligned16(hidden) || !aligned16(hidden_out)) return UP_ERR_ALIGN;
-  choose_geometry(&pb, cu_host, ks.cu_k_host);
+  choose_geometry(&pb, cu_host, ks.cu_k_host, workspace_bytes);
   if (pb.T > 0 && (workspace == nullptr || workspace_bytes < workspace_layout(pb).total)) return UP_ERR_WORKSPACE;
   if (pb.T > 0 && (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return UP_ERR_ALIGN;
   if ((st = score_impl(p, q, k, cu_dev, cu_host, ks, scores, workspace, workspace_bytes, stream, lse, lse_stride)) != UP_OK)
@@ -899,7 +906,8 @@ int uniprefill_fused_static(const up_params* p, const void* q, const void* k, co
                             void* stream) {
   // what the call needs, from the same closed forms as uniprefill_plan (host only)
   size_t need = 0;
-  const int st = plan_impl(p, cu_seqlens_host, nullptr, false, keep_ratio_host, nullptr, nullptr, &need);
+  const int st = plan_impl(p, cu_seqlens_host, nullptr, false, keep_ratio_host, nullptr, nullptr, &need,
+                           UNIPREFILL_STATIC_SCRATCH_BYTES);
   if (st != UP_OK) return st;
   if (need > (size_t)UNIPREFILL_STATIC_SCRATCH_BYTES) return UP_ERR_SCRATCH;
   void* ws = nullptr;

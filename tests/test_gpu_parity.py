@@ -387,6 +387,22 @@ def test_fused_head_dim_64_in_every_launch_geometry_bit_exact(name):
     _assert_fused_exact(w, b, oracle_run(w))
 
 
+def test_fused_head_dim_64_in_a_workspace_that_holds_the_256_key_form_only():
+    """Outputs of the smaller form are the same bits; the bytes beyond the workspace stay as they are."""
+    _say("fused head_dim 64, 2048 bytes less workspace")
+    batch = HEAD_64["whole_one_round_long_window"][0]
+    w = workloads.make_custom(name="hd64w", seed=24, keep_ratio=[0.4] * 2, hidden_dim=64, block_size=32, head_dim=64, **batch)
+    full, small = DeviceBatch(w), DeviceBatch(w)
+    small.ws_bytes -= 2048
+    small.workspace.fill_(0xA5)
+    full.fused()
+    small.fused()
+    got, want = small.results(), full.results()
+    for key in want:
+        np.testing.assert_array_equal(got[key], want[key], err_msg=key)
+    assert (small.workspace[small.ws_bytes:] == 0xA5).all() and small.canaries_intact()
+
+
 def test_scores_from_fp32_operands_head_dim_64():
     _say("score fp32 head_dim 64")
     w = workloads.make_custom(name="f32hd", seed=16, lengths=[1, 130, 0, 700, 2100], keep_ratio=[0.5] * 5,

@@ -29,8 +29,9 @@ def host_lib(tmp_path_factory):
     return ctypes.CDLL(lib)
 
 
-def geometry(lib, lengths, num_q_heads, num_kv_heads, n_obs, head_dim=64, earlier=None, qk_dtype=up.UP_BF16):
-    """((keys per work-group, split) of pass 1, the same of pass 2) of a score call, and its workspace bytes."""
+def geometry(lib, lengths, num_q_heads, num_kv_heads, n_obs, head_dim=64, earlier=None, qk_dtype=up.UP_BF16, less=0):
+    """((keys per work-group, split) of pass 1, the same of pass 2) of a score call given `less` bytes fewer than planned,
+    and the planned workspace bytes; None where the call finds its workspace too small."""
     cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
     cu_k = None if earlier is None else np.concatenate([[0], np.cumsum(np.add(lengths, earlier))]).astype(np.int32)
     ratio = np.full(len(lengths), 0.5, np.float32)
@@ -41,10 +42,14 @@ def geometry(lib, lengths, num_q_heads, num_kv_heads, n_obs, head_dim=64, earlie
     ws = ctypes.c_size_t(0)
     if earlier is None:
         assert lib.uniprefill_plan(ctypes.byref(p), host(cu), host(ratio), None, None, ctypes.byref(ws)) == 0
-        st = lib.uniprefill_score(ctypes.byref(p), dev, dev, dev, host(cu), dev, dev, ws, None)
+        room = ctypes.c_size_t(ws.value - less)
+        st = lib.uniprefill_score(ctypes.byref(p), dev, dev, dev, host(cu), dev, dev, room, None)
     else:
         assert lib.uniprefill_plan_chunked(ctypes.byref(p), host(cu), host(cu_k), host(ratio), None, None, ctypes.byref(ws)) == 0
-        st = lib.uniprefill_score_chunked(ctypes.byref(p), dev, dev, dev, host(cu), dev, host(cu_k), dev, dev, ws, None)
+        room = ctypes.c_size_t(ws.value - less)
+        st = lib.uniprefill_score_chunked(ctypes.byref(p), dev, dev, dev, host(cu), dev, host(cu_k), dev, dev, room, None)
+    if st == up.UP_ERR_WORKSPACE:
+        return None
     assert st == 0
     g = (ctypes.c_int32 * 4)()
     lib.stub_last_geometry(g)
@@ -71,3 +76,31 @@ def test_other_head_rows_take_pass_1s_key_block_in_both_passes(host_lib):
         for head_dim, dtype in ((128, up.UP_BF16), (256, up.UP_BF16), (64, up.UP_F32), (128, up.UP_F32)):
             g1, g2, _ = geometry(host_lib, lengths, 32, 8, 128, head_dim=head_dim, qk_dtype=dtype)
             assert g1 == g2 and (g1[0] == 256 or (head_dim == 128 and dtype == up.UP_BF16))
+
+
+def test_workspace_of_the_256_key_form_is_still_enough_where_512_keys_are_faster(host_lib):
+    """The partial column sums of 116002 tokens in two sequences take 228 * 512 doubles or 455 * 256."""
+    batch, pass1, pass2 = HEAD_64["whole_one_round_long_window"]
+    assert geometry(host_lib, **batch)[1] == (512, 1)
+    assert geometry(host_lib, **batch, less=2048)[1] == (256, 1)
+    assert geometry(host_lib, **batch, less=2048 + 256) is None
+    # nothing else has a smaller form
+    for name in ("whole_many_rounds", "context"):
+        assert geometry(host_lib, **HEAD_64[name][0], less=256) is None
+
+
+def test_static_scratch_takes_what_fits_at_256_keys(host_lib):
+    """A batch that needs 32 MiB + 2816 bytes at 512 keys and less than 32 MiB at 256 is not refused for its size (this
+    build has no device: the call ends there)."""
+    lengths = [19800] * 6
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    ratio = np.full(6, 0.5, np.float32)
+    assert geometry(host_lib, lengths, 32, 1, 521)[2] == up.STATIC_SCRATCH_BYTES + 2816
+    p = up.make_params(num_seqs=6, total_tokens=int(cu[-1]), block_size=64, n_obs=521, num_q_heads=32, num_kv_heads=1,
+                       head_dim=64, hidden_dim=64)
+    host, dev = (lambda a: ctypes.c_void_p(a.ctypes.data)), ctypes.c_void_p(1 << 20)
+    call = lambda: host_lib.uniprefill_fused_static(ctypes.byref(p), dev, dev, dev, dev, dev, host(cu), dev, host(ratio), dev, dev,
+                                                    dev, dev, None, None)
+    assert call() == up.UP_ERR_HIP
+    p.n_obs = 523                     # too large in either form
+    assert call() == up.UP_ERR_SCRATCH
